@@ -648,13 +648,27 @@ __device__ __forceinline__ void store_vec(S* dst, int N, int s, S vx, S vy, S vz
   }
 }
 
+// Products and sums kept apart, so that every kernel that inlines them rounds
+// alike.
+template <typename S>
+__device__ __forceinline__ S mul_only(S a, S b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+template <typename S>
+__device__ __forceinline__ S add_only(S a, S b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
 // Moments of the pulled populations, the velocity u = (jbar + F/2)/rho
 // (handed to `emit`) and, with COLLIDE, the collision with the mode noise nk,
 // written to a.f_out.
 // GHOST: the ghost modes keep gamma_g m_g (omega_ghost != 1).
 template <typename S, bool DEV, int Q, bool GHOST, bool COLLIDE, int NT, typename Emit>
 __device__ __forceinline__ void lb_update(const LBArgs<S>& a, int s, const S (&fv)[Q],
-                                          const S (&F)[3], S (&nk)[kModeSlots<Q>], Emit emit) {
+                                          const S (&F)[3], const S (&nk)[kModeSlots<Q>],
+                                          Emit emit) {
   using L = Lat<Q>;
   constexpr int D = L::D;
   constexpr int NR = Q - D - 1;
@@ -725,14 +739,17 @@ __device__ __forceinline__ void lb_update(const LBArgs<S>& a, int s, const S (&f
   const S qtr = qxx + qyy + qzz;
   const S jsx = jx + F[0], jsy = jy + F[1], jsz = jz + F[2];
 
-  // Scale the amplitudes into integer-basis units (and add gamma_g m_g).
+  // The amplitudes (with gamma_g m_g), and in integer-basis units.  In copies: nk
+  // is the caller's, who may hold it over several sites.
+  S md[NR], amp[NR];
   static_for<NR>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     constexpr double sc = kSB<Q, D + 1 + k>;
     if constexpr (GHOST && k >= L::NSTRESS)
-      nk[k] = S(sc) * (nk[k] + a.gamma_g * (S(sc) * ghost[k]));
+      md[k] = fma(a.gamma_g, S(sc) * ghost[k], nk[k]);
     else
-      nk[k] = S(sc) * nk[k];
+      md[k] = nk[k];
+    amp[k] = mul_only<S>(S(sc), md[k]);
   });
 
   static_for<Q>([&](auto ic) {
@@ -753,7 +770,11 @@ __device__ __forceinline__ void lb_update(const LBArgs<S>& a, int s, const S (&f
     static_for<NR>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       constexpr int c = kIB<Q, D + 1 + k, i>;
-      if constexpr (c != 0) nz += S(c) * nk[k];
+      // spelled out, so that every kernel that inlines it rounds alike
+      if constexpr (c == 1 || c == -1)
+        nz = fma(S(c * kSB<Q, D + 1 + k>), md[k], nz);
+      else if constexpr (c != 0)
+        nz = fma(S(c), amp[k], nz);
     });
     // Populations are streamed: written once here, read once by the next
     // step, so large lattices bypass the caches with them (non-temporal).
@@ -1421,18 +1442,6 @@ struct FluxArgs {
   S* phi;          // phi^1
   S* rate;         // R
 };
-
-// Products and sums kept apart, so that every form of the kernel rounds alike.
-template <typename S>
-__device__ __forceinline__ S mul_only(S a, S b) {
-#pragma clang fp contract(off)
-  return a * b;
-}
-template <typename S>
-__device__ __forceinline__ S add_only(S a, S b) {
-#pragma clang fp contract(off)
-  return a + b;
-}
 
 template <typename S, bool DEV, int Q, int NT, bool WALLS>
 __device__ __forceinline__ void uend_stage_body(const LBArgs<S>& la, const FluxArgs<S>& a,
