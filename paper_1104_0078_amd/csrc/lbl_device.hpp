@@ -232,10 +232,10 @@ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, uint32_t k0, uint32_t k1
 
 enum : uint32_t { kTagLB = 0, kTagSMOL = 1, kTagInit = 2 };
 
-// The tables of the FP64 normals in LDS, filled by a block of 256 threads, 16
-// bytes each: `fetch` issues the load (ahead of a kernel's own first loads),
-// `store` waits for it; a barrier must follow before the first draw.  FP32 uses
-// none.
+// The tables of the FP64 normals in LDS, filled by a block of 256 threads, a row
+// and an offset each: `fetch` issues the loads (ahead of a kernel's own first
+// loads), `store` waits for them; a barrier must follow before the first draw.
+// FP32 uses none.
 __device__ const bm::Tables kNormalTables = bm::kTables;
 
 template <typename S>
@@ -250,13 +250,19 @@ template <>
 struct NormalTables<double> {
   static constexpr bool kUsed = true;
   bm::Tables t;
-  using Part = bm::Row;
-  static_assert(sizeof(bm::Tables) == 256 * sizeof(bm::Row), "one row per thread");
+  struct Part {
+    bm::Row row;
+    int mid;
+  };
+  static_assert(sizeof(bm::Tables) == 256 * sizeof(bm::Row) + 128 * sizeof(int),
+                "one row per thread");
   __device__ __forceinline__ static Part fetch(int tid) {
-    return reinterpret_cast<const bm::Row*>(&kNormalTables)[tid];
+    return Part{reinterpret_cast<const bm::Row*>(&kNormalTables)[tid],
+                kNormalTables.mid[tid & 127]};
   }
   __device__ __forceinline__ void store(int tid, const Part& p) {
-    reinterpret_cast<bm::Row*>(&t)[tid] = p;
+    reinterpret_cast<bm::Row*>(&t)[tid] = p.row;
+    if (tid < 128) t.mid[tid] = p.mid;
   }
 };
 
@@ -300,7 +306,7 @@ struct Normal4<double> {
                                               double& zb) {
     const double r = sqrt_radius(bm::neg2_log(static_cast<double>(ka) + 0.5, t.t.log));
     double s, c;
-    bm::sincos_rows(kb, t.t.cs, &s, &c);
+    bm::sincos_rows(kb, t.t, &s, &c);
     za = r * c;
     zb = r * s;
   }
