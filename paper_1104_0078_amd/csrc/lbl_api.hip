@@ -118,6 +118,14 @@ int hip_check(lbl_sim* s, hipError_t e, const char* what) {
   return fail(s, LBL_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// An allocation that failed leaves the runtime's last error set, here or in the
+// injected allocator, and the next launch check would take it for its own:
+// clear it, as the caller learns of the failure from the pointer.
+void* allocated(void* ptr) {
+  if (!ptr) (void)hipGetLastError();
+  return ptr;
+}
+
 void* dev_alloc(lbl_sim* s, size_t bytes) {
   void* ptr = nullptr;
   if (bytes == 0) bytes = 8;
@@ -126,7 +134,7 @@ void* dev_alloc(lbl_sim* s, size_t bytes) {
   } else if (hipMalloc(&ptr, bytes) != hipSuccess) {
     ptr = nullptr;
   }
-  if (ptr) s->owned.push_back(ptr);
+  if (allocated(ptr)) s->owned.push_back(ptr);
   return ptr;
 }
 
@@ -1786,8 +1794,8 @@ namespace {
 
 void* pool_alloc(lbl_pool* pl, size_t bytes) {
   void* ptr = nullptr;
-  if (pl->env.alloc) return pl->env.alloc(pl->env.ctx, bytes, pl->stream);
-  return hipMalloc(&ptr, bytes) == hipSuccess ? ptr : nullptr;
+  if (pl->env.alloc) return allocated(pl->env.alloc(pl->env.ctx, bytes, pl->stream));
+  return allocated(hipMalloc(&ptr, bytes) == hipSuccess ? ptr : nullptr);
 }
 
 void pool_free(lbl_pool* pl, void* ptr) {
@@ -2333,7 +2341,7 @@ int lbl_diag_normals(int32_t device, int32_t precision, uint64_t seed, uint32_t 
   if (hipSetDevice(device) != hipSuccess) return LBL_E_DEVICE;
   const size_t bytes = sizeof(double) * static_cast<size_t>(n_sites) * n_slots;
   double* d = nullptr;
-  if (hipMalloc(&d, bytes) != hipSuccess) return LBL_E_NOMEM;
+  if (!allocated(hipMalloc(&d, bytes) == hipSuccess ? d : nullptr)) return LBL_E_NOMEM;
   const int n = static_cast<int>(n_sites);
   const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
   if (precision == LBL_FP64)
