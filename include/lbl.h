@@ -340,7 +340,8 @@ int lbl_get_schedule(const lbl_sim *sim, lbl_schedule *out);
  * FP64, [site][slot]) receives the normal of slot s (Philox block s/4, lane
  * s%4) of the counter (site0 + i, step, block, tag) under key seed, computed
  * on `device` with the transform of the given storage (LBL_FP64 or
- * LBL_FP32DEV).  Synchronous; allocates and frees its own device memory.
+ * LBL_FP32DEV); in FP64 the LB stream's (tag 0) with the polynomials of the
+ * per-site LB pass, the others' from the tables of the other kernels.  Synchronous; allocates and frees its own device memory.
  * For tests of the generator against independent implementations.
  * Errors: LBL_E_INVAL (NULL dst, n_sites outside 1..2^24, n_slots outside
  * 1..64, unknown precision), LBL_E_NOMEM, LBL_E_DEVICE. */

@@ -2192,7 +2192,9 @@ __global__ __launch_bounds__(kBX* kBY) void k_mu_w(Geom g, Coef<S> c, const S* _
 // Initial state and observables (one thread per site, 1-D grid).
 // ---------------------------------------------------------------------------
 // Diagnostics: normals of Philox blocks 0 .. nblk-1 at sites site0 + i,
-// written as FP64 [site][slot] (slots beyond nslots dropped).
+// written as FP64 [site][slot] (slots beyond nslots dropped).  The LB stream's with
+// the functions of the per-site LB pass, the others' from the tables (which the
+// D2Q9 halves use for both).
 template <typename S>
 __global__ __launch_bounds__(256) void k_diag_normals(uint32_t site0, int n, int nslots, uint32_t step,
                                                        uint32_t tag, uint32_t k0, uint32_t k1,
@@ -2203,8 +2205,11 @@ __global__ __launch_bounds__(256) void k_diag_normals(uint32_t site0, int n, int
   if (i >= n) return;
   for (int b = 0; 4 * b < nslots; ++b) {
     S z[4];
-    Normal4<S>::gen(site0 + static_cast<uint32_t>(i), step, static_cast<uint32_t>(b), tag, k0, k1,
-                    tables, z);
+    const uint32_t site = site0 + static_cast<uint32_t>(i), block = static_cast<uint32_t>(b);
+    if (tag == kTagLB)
+      Normal4<S>::gen(site, step, block, tag, k0, k1, PolyNormals{}, z);
+    else
+      Normal4<S>::gen(site, step, block, tag, k0, k1, tables, z);
     for (int l = 0; l < 4 && 4 * b + l < nslots; ++l)
       out[static_cast<size_t>(i) * nslots + 4 * b + l] = static_cast<double>(z[l]);
   }
