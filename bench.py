@@ -72,7 +72,20 @@ def noise_in_velocity_pass(w, schedule):
             and not (w["smol"] == 0 and w.get("fd_noise", 0) == 1))
 
 
-def kernel_alg_bytes_per_site(name, w, rk=2, schedule=None):
+def step_form(ktimes, steps):
+    """The form of the steps that gave these kernel times: "halves" (the two
+    launches of the D2Q9 Heun step), "flux" (the FV Heun step in 3-D, whose
+    velocity pass takes the first stage: one k_stage launch a step), else
+    "phases"."""
+    launches = {name: n for name, n, _ in ktimes}
+    if "k_half1" in launches:
+        return "halves"
+    if launches.get("k_uend", 0) == launches.get("k_stage", 0) == steps > 0:
+        return "flux"
+    return "phases"
+
+
+def kernel_alg_bytes_per_site(name, w, rk=2, schedule=None, form="phases"):
     """Algorithmic bytes per site of one launch of each kernel: every field
     the kernel needs read once and every field it produces written once (no
     halo re-reads); b bytes per stored value, d dimensions.
@@ -86,15 +99,29 @@ def kernel_alg_bytes_per_site(name, w, rk=2, schedule=None):
       k_stage: read the stage input, the velocity (d values) and the noise,
                write the output; the final Heun stage also reads psi^n
                (mean over the two launches of a step):      (3 + d) b + b/2.
-    The Heun step of FV on 3-D lattices takes its first stage in k_uend, which
-    then also reads the flux that k_lb writes for u^n and writes the stage's
-    output and rate ((2 + d) b, less the noise's b); its one k_stage launch
-    moves (3 + d) b.  Neither is counted here, nor the two launches of the D2Q9
-    step."""
+    In the "flux" form (step_form) k_lb writes the flux (d values) for u^n and
+      k_uend:  takes the first stage too: it also reads the flux and writes
+               the stage's output and rate, and no noise:   (Q + 4 + 2d) b;
+      k_stage: reads the stage's output and rate and the velocity, writes
+               psi:                                         (3 + d) b;
+      k_prep:  mu alone:                                    2 b.
+    In the "halves"
+      k_half1: pulls the Q populations, reads psi, writes the populations, the
+               stage's output and rate:                     (2Q + 3) b;
+      k_half2: pulls the Q populations, reads psi, the stage's output and rate,
+               writes psi:                                  (Q + 4) b."""
     b = 8 if w["precision"] == 0 else 4
     d = 2 if w["lattice"] == 9 else 3
     q = w["lattice"]
     fused = noise_in_velocity_pass(w, schedule)
+    if form == "flux" and name.startswith("k_uend"):
+        return (q + 4 + 2 * d) * b
+    if form == "flux" and name.startswith("k_stage"):
+        return (3 + d) * b
+    if name.startswith("k_half1"):
+        return (2 * q + 3) * b
+    if name.startswith("k_half2"):
+        return (q + 4) * b
     if name.startswith("k_lb"):
         return (2 * q + 2 + d) * b
     if name.startswith("k_uend"):
@@ -614,7 +641,8 @@ def main():
     per_kernel = {}
     for kname, klaunch, kms in r["ktimes"]:
         avg_s = kms / klaunch / 1e3
-        kb = kernel_alg_bytes_per_site(kname, w, schedule=r["schedule"])
+        kb = kernel_alg_bytes_per_site(kname, w, schedule=r["schedule"],
+                                       form=step_form(r["ktimes"], args.steps))
         if kb is None:
             continue
         achieved = kb * N / avg_s / 1e9
