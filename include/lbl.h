@@ -318,12 +318,16 @@ int lbl_timing_read(lbl_sim *sim, lbl_kernel_time *out, int max_entries, int *n_
  * the velocity pass takes the first stage with it, so that overlap 1 is 0.
  * Default: the widest width up to 256
  * that fits nx, xcd_swizzle 2 (3 where the LB pass gains from it too: 3-D
- * lattices with planes of up to 128 x 256 sites, and populations too large for
- * the caches that are no whole number of 128-byte lines), zc per kernel from its
+ * lattices with planes of up to 128 x 256 sites, in FP64 only where the row blocks
+ * tile the plane, and not planes of a power of two sites with nz no multiple of 8;
+ * and populations too large for the caches that are no whole number of 128-byte
+ * lines), zc per kernel from its
  * occupancy (the stage's by a count of the planes its blocks march in each round
- * of resident blocks; the preparation kernel's and the velocity pass's blocks
- * fill two rounds; chunks below 8 planes only where the lattice would leave
- * the device idle), overlap 3.  The z-marching stress pass of force_form STRESS (FV, 3-D) keeps
+ * of resident blocks; the velocity pass that takes the first stage fills four
+ * rounds of up to four blocks a compute unit with at least 4 planes a block; the
+ * preparation kernel and the other velocity passes fill two rounds with at least
+ * 8; fewer planes only where the lattice would leave the device idle),
+ * overlap 3.  The z-marching stress pass of force_form STRESS (FV, 3-D) keeps
  * its own default (two rounds) whatever zc is.  Errors: LBL_E_INVAL (NULL,
  * unsupported width, zc < 0, overlap not 0, 1, 2 or 3). */
 typedef struct lbl_schedule {

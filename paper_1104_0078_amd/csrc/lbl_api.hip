@@ -861,7 +861,7 @@ struct Impl {
   // full coupling with the default force and noise drawn in real space:
   // the faster form at every size: 64^2 FD FP64 25.0 -> 11.4 us a step (five
   // launches of 3-5 us each), 1024x128 FV FP32 27.5 -> 12.2, 4096^2 FD FP64
-  // 1400 -> 1024 (49 -> 34 values moved per site).
+  // 1400 -> 1045 (49 -> 34 values moved per site).
   // FV on 3-D lattices takes Heun under full coupling in the flux form
   // (k_uend_stage).  The stress-divergence force does not need mu, which the flux
   // form computes for its J, so there it gains only the launch and the stage's

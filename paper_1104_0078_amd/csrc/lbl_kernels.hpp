@@ -555,11 +555,12 @@ __device__ __forceinline__ bool beyond_wall(const Geom& g, int y, int z, int dy,
 // 128-byte lines: the runs of two blocks then share a line in most planes, and
 // a line stored in two non-temporal parts goes out twice.  Stored through the
 // caches, with the blocks of neighbouring runs on one XCD, its parts meet in
-// L2.  (The velocities, three planes of 22, stay streamed.)  LB pass + velocity
-// pass, ps a site, all streamed against loads only in XCD order: FP64 181^3 84 + 58 against 70 + 61, 205x157x131 81 + 55 against
-// 66 + 60, FP32 181^3 51 + 28 against 34 + 32, 205x157x131 49 + 29 against 33 +
-// 31; whole lines FP64 256^3 64 + 49 against 66 + 50, FP32 30 + 24 against
-// 31 + 26.
+// L2.  So are the LB pass's velocities or flux; the velocity passes take kStream on
+// such lattices too and stream theirs, three planes of 22.  LB pass + velocity
+// pass, ps a site, all streamed against loads only in XCD order: FP64 181^3
+// 84 + 58 against 70 + 61, 205x157x131 81 + 55 against 66 + 60, FP32 181^3 51 + 28
+// against 34 + 32, 205x157x131 49 + 29 against 33 + 31; whole lines FP64 256^3
+// 64 + 49 against 66 + 50, FP32 30 + 24 against 31 + 26.
 constexpr double kStreamBytes = 256.0 * 1024 * 1024;
 enum : int { kCached = 0, kStream = 1, kStreamLoads = 2 };
 __host__ inline bool whole_lines(size_t ssize, int64_t N) {
@@ -1270,7 +1271,7 @@ __device__ __forceinline__ void prep_fd_body(const PrepArgs<S>& a, int bx, int b
   // those of l_y = -1.  (Looping the threads over whole halo sites drew 6 wave
   // passes of NB blocks for 4 of output, two waves twice as long as the rest;
   // now NB + 1 blocks a wave.  205x157x131 FP64, with the tables of the normals:
-  // velocity pass with the link noise 375 -> 253 us.)
+  // velocity pass with the link noise 375 -> 253 us; since then 238.)
   constexpr int kUp0 = 0, kUpN = D == 3 ? 3 : 1;      // blocks of links with l_y = +1
   constexpr int kDown0 = D == 3 ? 1 : 0, kDownN = D == 3 ? 3 : 1;
   static_assert(link_blocks_ok<Q>(kUp0, kUpN, kDown0, kDownN), "blocks of the halo rows");
@@ -1425,10 +1426,12 @@ __global__ __launch_bounds__(kTX* kTY) void k_uend_noise(LBArgs<S> la, PrepArgs<
 // A stage kernel of its own recomputes mu and J from psi with a three-site
 // halo and reads u^n, psi^n and N^n again.  256^3 FP64: velocity pass with the
 // noise 704 us + first stage 255 us -> 865 us; FP32 320 + 158 -> 417 us; the
-// second stage, without psi^n, 262 -> 244 and 160 -> 149 us.  (Since then 805 us
-// in FP64, with PlaneNbr and shorter z-chunks.)
-// The pass is bound by its memory traffic (populations in runs of 256 sites of
-// a plane, J with a one-site halo) and, in FP64, by the issue of the normals.
+// second stage, without psi^n, 262 -> 244 and 160 -> 149 us.  (Since then 805 to
+// 820 us in FP64, with PlaneNbr and shorter z-chunks.)
+// At 256^3 the pass is bound by its memory traffic (populations in runs of 256
+// sites of a plane, J with a one-site halo): 318 of 232 B a site at 6.5 TB/s in FP64
+// and 171 of 116 at 7.0 in FP32; on smaller lattices by latency (128^3 FP64 4.5
+// TB/s, VALU 33% busy).
 // J and xi sit in LDS as pairs, so that each tap of the two folds is one read.
 template <typename S>
 struct FluxArgs {

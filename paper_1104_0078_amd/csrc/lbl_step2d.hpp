@@ -22,10 +22,10 @@
 // (4096^2 FP64, 64 x 8, half 1 + half 2: 714 + 477 -> 675 + 380 us; FP32
 // 357 + 263 -> 328 + 215; 64^2 FP64, 32 x 8, 13.7 -> 11.8 us a step).  The
 // pulls are cached, as a ring is part of four other tiles.
-// Measured (half 1 + half 2, us): 64^2 FD FP64 9.6 + 8.2 timed singly (11.4 a
-// step back to back), 1000^2 FD FP64 47 + 22, 4096^2 FD FP64 645 + 373 (4.7
-// and 5.4 TB/s of 91 + 88 and 113 + 8 B a site), FP32 320 + 216.  What is
-// left of half 1 in FP64 is issue: about 1900 instructions a thread.
+// Measured (half 1 + half 2, us): 64^2 FD FP64 9.1 + 6.8 timed singly (11.4 a
+// step back to back), 1000^2 FD FP64 47 + 22, 4096^2 FD FP64 693 + 376 (4.3
+// and 5.4 TB/s of 92 + 88 and 113 + 8 B a site), FP32 334 + 214.  What is left of
+// half 1 in FP64 is issue: 1922 instructions a thread, VALU 75% busy.
 #pragma once
 
 #include "lbl_kernels.hpp"
